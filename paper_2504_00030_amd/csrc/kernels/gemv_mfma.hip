@@ -261,7 +261,9 @@ __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(
 //   first waves; the test is on the scalar wave index, so every branch around a matrix instruction stays scalar.
 constexpr int persist_burst(int tpw, int frags) {
     // tiles per burst of loads: a divisor of the wave's tiles per group, at most 8 KiB per wave, 4 KiB where the x
-    // fragments already take 64 registers and 2 KiB where they take 80 (a deeper burst there spills)
+    // fragments already take 64 registers and 2 KiB where they take 80 (a deeper burst there spills more: at this one
+    // the QKV and LM-head epilogues spill 13 and 36 registers with both terms at K = 5120, a case that gemv_ksplit_k
+    // serves, and 4 and 19 at K = 4096)
     const int cap = frags >= 20 ? 2 : (frags >= 16 ? 4 : 8);
     int ub = 1;
     for (int d = 1; d <= cap; ++d)
