@@ -684,6 +684,9 @@ bool gemm_mfma_serves(int epi, int Ntot, int K, int R) {
 // k-tile whatever its rows (load latency it cannot hide: 0.57 us for the narrow block alone on a compute unit, 1.17
 // us per pair sharing one; 1.0 / 1.7 us for the wide block), the blocks run in rounds of 512, a split of K
 // adds its summing pass, and the live rows of a block cost about 0.075 us each (x rows fetched, epilogue rows).
+// The constants are those of launches that repeat one matrix, which the memory-side cache (256 MB) then holds; with
+// weights from HBM the lower blocks take longer.  28672 x 4096 at 32 / 96 rows: 48 / 74 us here, 47 / 74-77 measured on one
+// matrix, 65 / 92-95 on matrices in turn; 27648 x 5120 (283 MB) at 32 rows: 58 here, 75 / 79 measured.
 float gemm_mfma_estimate_us(int Ntot, int K, int R, size_t ws_bytes, bool q8) {
     const int m_blocks = (R + 127) / 128, KT = K / 32;
     const float rows_us = 0.075f * std::min(R, 128);
