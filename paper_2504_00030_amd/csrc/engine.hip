@@ -229,9 +229,6 @@ bool model_on_matrix_cores(const spec_config &g, const spec_shape &s) {
            s.vocab % 16 == 0 && (s.head_dim / 2) % 8 == 0 && d % 16 == 0;
 }
 
-// Rows of one prompt-ingestion launch (all sequences together).  A model on the matrix cores whose attention
-// also runs on them ingests through the dense-contraction kernels, PREFILL_GEMM_ROWS rows at a time; otherwise
-// PREFILL_ROWS per sequence (the plain attention kernel holds at most 128 rows of a sequence).
 // Whether the attention of a model on the matrix cores runs on the matrix-core attention kernels as well.
 bool attention_on_matrix_cores(const spec_config &g, const spec_shape &s) {
     const int hd = s.head_dim;
@@ -239,6 +236,9 @@ bool attention_on_matrix_cores(const spec_config &g, const spec_shape &s) {
     return g.page_tokens % 4 == 0 && (hd == 32 || hd == 64 || hd == 128) && (g.max_seq + chunk - 1) / chunk <= ATT_NC_MAX;
 }
 
+// Rows of one prompt-ingestion launch (all sequences together).  A model on the matrix cores whose attention
+// also runs on them ingests through the dense-contraction kernels, PREFILL_GEMM_ROWS rows at a time; otherwise
+// PREFILL_ROWS per sequence (the plain attention kernel holds at most 128 rows of a sequence).
 int ingest_rows(const spec_config &g, const spec_shape &s) {
     const bool attn_mc = attention_on_matrix_cores(g, s);
     if (model_on_matrix_cores(g, s) && attn_mc && s.d_model / 16 <= SSQ_STRIDE) return std::max(PREFILL_GEMM_ROWS, g.batch);
@@ -458,8 +458,8 @@ int launch_proj(spec_ctx *c, ModelRT &m, GemvArgs a, int epi, const void *tiled,
     // on the row count.  The weight-streaming kernel beyond the 16 rows of its persistent form is bound by what a
     // compute unit fetches: per 16-row group of W its 32 K bytes (16 K with 8-bit weights) plus the 4 K bytes of
     // each row of x, shared by the groups of a workgroup, at about 38 GB/s per compute unit (measured on the 8B and
-    // 1B shapes at 17-128 rows: this model and the dense estimate pick the faster kernel to within 0.5 % of the
-    // summed times).  Whichever estimate is lower runs; beyond 128 rows the dense kernel is the only one.
+    // 1B shapes at 17-128 rows, each launch repeated on one matrix: this model and the dense estimate pick the faster
+    // kernel to within 0.5 % of the summed times).  Whichever estimate is lower runs; beyond 128 rows the dense kernel is the only one.
     bool dense = m.mfma_ok && gemm_mfma_serves(epi, Ntot, a.K, a.R) && a.x_mul == 1 && a.x_add == 0;
     if (dense && a.R <= 128) {
         const int ng = gemv_mfma_groups_per_wg(epi, Ntot, a.K, a.R, 0, m.q8);
